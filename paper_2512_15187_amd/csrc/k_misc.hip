@@ -218,8 +218,12 @@ __global__ __launch_bounds__(256) void rank_kernel(RankArgs ra, int n) {
 // per wave) against tiles of 2048 depths staged in LDS.  For a chunk of 64 j
 // entirely below the wave's members, "before" is d_j >= d_i; entirely above,
 // d_j > d_i; only the chunk that holds the members themselves needs the
-// index test.  Padding past n is NaN, which compares false.
+// index test.  Padding past n is NaN, which compares false.  A depth that is NaN
+// is taken as +infinity, so that the ranks are a permutation whatever the depths
+// hold (and NaN comes first, as in the sorting ranks below).
 constexpr int kRankTile = 2048;
+
+__device__ __forceinline__ double rank_value(double d) { return fmin(d, __builtin_inf()); }
 
 template <int MPW>
 __global__ __launch_bounds__(256) void rank_lds_kernel(RankArgs ra, int n) {
@@ -231,13 +235,19 @@ __global__ __launch_bounds__(256) void rank_lds_kernel(RankArgs ra, int n) {
   int r[MPW];
 #pragma unroll
   for (int q = 0; q < MPW; ++q) {
-    di[q] = (i0 + q < n) ? d[i0 + q] : 0.0;
+    di[q] = (i0 + q < n) ? rank_value(d[i0 + q]) : 0.0;
     r[q] = 0;
   }
   for (int t0 = 0; t0 < n; t0 += kRankTile) {
     __syncthreads();
-    for (int k = threadIdx.x; k < kRankTile; k += 256)
-      tile[k] = (t0 + k < n) ? d[t0 + k] : __builtin_nan("");
+    double v[kRankTile / 256];   // (loaded together)
+#pragma unroll
+    for (int c = 0; c < kRankTile / 256; ++c) v[c] = d[min(t0 + 256 * c + (int)threadIdx.x, n - 1)];
+#pragma unroll
+    for (int c = 0; c < kRankTile / 256; ++c) {
+      const int k = 256 * c + threadIdx.x;
+      tile[k] = (t0 + k < n) ? rank_value(v[c]) : __builtin_nan("");
+    }
     __syncthreads();
     const int tend = min(kRankTile, n - t0);
     // chunks [0, cb) lie before every member of the wave, [ca, nc) after
