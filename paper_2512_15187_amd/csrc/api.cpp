@@ -133,7 +133,7 @@ pid_status resolve_scheme(const pid_ensemble* e, int kind, int gemm, int* scheme
 
 // Extra workspace after the kernels' own: depth scratch (for ranks; two
 // arrays for the combined call), the validation flag, and the scratch of the
-// sorting ranks (more than 2048 members).
+// sorting ranks (more than kRankCompareN members).
 size_t extra_bytes(int64_t n, int ndepth = 1) {
   return ((size_t)n * 8 * ndepth + 255) / 256 * 256 + 256 + 256 + (size_t)ndepth * pidk::rank_scratch_bytes(n);
 }

@@ -277,7 +277,7 @@ __global__ __launch_bounds__(256) void rank_lds_kernel(RankArgs ra, int n) {
   }
 }
 
-// Ranks by sorting, for more than 16384 members when the caller's workspace
+// Ranks by sorting, for more than kRankCompareN members when the caller's workspace
 // provides the scratch (rank_scratch_bytes per depth array).  The order of
 // the definition, "j comes before i" iff d_j > d_i or (d_j == d_i and j < i),
 // is the ascending order of the pairs (key(d_j), j) with key(d) decreasing in
@@ -381,11 +381,7 @@ static RankSort carve_rank_sort(void* scratch, int64_t n, int arrays) {
 }
 
 static void launch_rank_kernel(const RankArgs& ra, int64_t n, int arrays, hipStream_t st, void* scratch) {
-  // sorting costs about 40 us of barriers and launches whatever n; comparing all
-  // pairs grows with n^2 (whole PID-mean calls, m = 256, sorted against
-  // compared: n = 2,100 67 and 36 us, 10,000 102 and 84, 20,000 135 and 136,
-  // 40,000 176 and 261)
-  if (n > 16384 && scratch) {
+  if (n > kRankCompareN && scratch) {
     const RankSort rs = carve_rank_sort(scratch, n, arrays);
     const unsigned nb = (unsigned)((n + kSortTile - 1) / kSortTile);
     hipLaunchKernelGGL(rank_tile_sort, dim3(nb, arrays), 1024, 0, st, ra, rs, (int)n);

@@ -159,12 +159,17 @@ hipError_t launch_pid_pairs(const PairsPlan& p, const pid_ensemble& e, int iso_k
 // ---------------------------------------------------------------- misc
 hipError_t launch_extract(const pid_ensemble& e, int iso_kind, const ExtractHost& ex, void* u_out,
                           int out_dtype, hipStream_t st);
-// Scratch bytes per depth array of the sorting ranks (0: n <= 2048, ranked
-// directly).
+// Up to this many members are ranked by comparing all pairs of depths, more by
+// sorting where the caller has the scratch.  Sorting costs about 40 us of barriers
+// and launches whatever n; comparing grows with n^2 (whole PID-mean calls, m =
+// 256, sorted against compared: n = 2,100 67 and 36 us, 10,000 102 and 84, 20,000
+// 135 and 136, 40,000 176 and 261).
+constexpr int64_t kRankCompareN = 16384;
+// Scratch bytes per depth array of the sorting ranks (0 up to kRankCompareN
+// members).
 size_t rank_scratch_bytes(int64_t n);
-// Ranks (and order) of depth; with scratch (rank_scratch_bytes(n) bytes per
-// array) more than 2048 members are ranked by sorting, otherwise by direct
-// comparison.
+// Ranks (and order) of depth.  scratch: rank_scratch_bytes(n) bytes per array,
+// or null (then compared whatever n).
 hipError_t launch_rank(const double* depth, int64_t n, int32_t* rank, int32_t* order, hipStream_t st,
                        void* scratch = nullptr);
 // Both rankings of pid_both in one launch.
