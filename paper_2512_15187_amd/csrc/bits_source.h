@@ -38,6 +38,18 @@ __device__ __forceinline__ uint32_t low_bits16(uint4 v) {
   return lo | (hi << 8);
 }
 
+// Bit k of the result: whether byte k of v is nonzero.  (v_lerp_u8 averages
+// bytes: (b + 255) / 2 has its highest bit set exactly for b >= 1.)
+__device__ __forceinline__ uint32_t nz16(uint4 v) {
+  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  uint32_t t[2] = {0u, 0u};
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    t[k >> 1] = __builtin_amdgcn_udot4(__builtin_amdgcn_lerp(w[k], ~0u, 0u) & 0x80808080u,
+                                       (k & 1) ? 0x80402010u : 0x08040201u, t[k >> 1], false);
+  return (t[0] | (t[1] << 8)) >> 7;
+}
+
 // P (8 bit planes of counts) += c (4 planes).
 __device__ __forceinline__ void add4(uint32_t (&P)[8], const uint32_t (&c)[4]) {
   uint32_t cy = 0u;
@@ -86,7 +98,7 @@ struct SrcValues {
   }
   static __device__ __forceinline__ uint32_t bits(const Vec16<T>& v, const Extract& ex) {
     if constexpr (!STEP) {
-      return low_bits16(__builtin_bit_cast(uint4, v));
+      return nz16(__builtin_bit_cast(uint4, v));
     } else {
       uint32_t w = 0u;
 #pragma unroll
@@ -159,7 +171,7 @@ struct SrcValues {
   }
 };
 
-// U8 0/1 masks whose rows are not 4-byte aligned (16-byte loads there cost 5-8 %
+// U8 masks (a nonzero byte counts as 1) whose rows are not 4-byte aligned (16-byte loads there cost 5-8 %
 // more): the chunk is read as 16-byte blocks aligned down from its first byte,
 // a bytes (0..15) before it; a block holds points 16k - a .. 16k - a + 15, so a
 // lane's 16 points are the top 16 - a bits of its block's and the low a bits of
@@ -174,7 +186,7 @@ struct SrcBytes : SrcValues<uint8_t, false> {
     return Raw{bp[lane], bp[64 + lane], bp[a != 0 ? 128 : 127], a};
   }
   __device__ __forceinline__ void words(const Raw& r, const Extract&, uint32_t (&b)[1]) const {
-    const int hA = (int)low_bits16(r.a), hB = (int)low_bits16(r.b), hC = (int)low_bits16(r.c);
+    const int hA = (int)nz16(r.a), hB = (int)nz16(r.b), hC = (int)nz16(r.c);
     const int b0 = __builtin_amdgcn_readfirstlane(hB);
     const uint32_t nA = (uint32_t)__builtin_amdgcn_update_dpp(b0, hA, 0x130, 0xF, 0xF, false);   // wave_shl:1
     const uint32_t nB = (uint32_t)__builtin_amdgcn_update_dpp(hC, hB, 0x130, 0xF, 0xF, false);

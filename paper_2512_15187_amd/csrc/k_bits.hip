@@ -31,19 +31,6 @@
 namespace pidk {
 
 // ---------------------------------------------------------------- U8 -> bits
-// Bit k of the result: whether byte k of v is nonzero (each byte's bits are
-// ORed into its lowest one first).
-__device__ __forceinline__ uint32_t nz16(uint4 v) {
-  uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    w[k] |= w[k] >> 4;
-    w[k] |= w[k] >> 2;
-    w[k] |= w[k] >> 1;
-  }
-  return low_bits16(make_uint4(w[0], w[1], w[2], w[3]));
-}
-
 // A chunk of 2048 points of a row is 64 words; lane l holds word l / 2
 // (even l) or 32 + l / 2 (odd l) of it.
 __device__ __forceinline__ int chunk_word(int lane) { return (lane & 1) ? 32 + (lane >> 1) : (lane >> 1); }
