@@ -47,6 +47,7 @@ def _compile(src: str):
         for f in os.listdir(tmp):
             if f.endswith(f"-{ARCH}.s"):
                 check_m0(os.path.join(tmp, f))
+                check_dispatch_packet(os.path.join(tmp, f))
     shutil.rmtree(tmp, ignore_errors=True)
     return obj, r.stderr
 
@@ -65,6 +66,21 @@ def check_m0(asm_path: str):
                 bad.append(l)
     if bad:
         raise RuntimeError(f"{os.path.basename(asm_path)}: M0 used outside the LDS loads: {bad[:5]}")
+
+
+def check_dispatch_packet(asm_path: str):
+    """Fail if a kernel reads its dispatch packet, which lies in host memory
+    (about 10 us per launch): the compiler does so to place a local array that
+    is indexed at run time in LDS.  No kernel here asks for it by itself."""
+    kernel, bad = "", []
+    for l in open(asm_path):
+        w = l.split()
+        if w[:1] == [".amdhsa_kernel"]:
+            kernel = w[1]
+        elif w[:2] == [".amdhsa_user_sgpr_dispatch_ptr", "1"]:
+            bad.append(kernel)
+    if bad:
+        raise RuntimeError(f"{os.path.basename(asm_path)}: kernels that read the dispatch packet: {bad[:5]}")
 
 
 def resource_report(remarks: str):

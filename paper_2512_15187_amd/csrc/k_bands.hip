@@ -150,7 +150,12 @@ __global__ __launch_bounds__(256) void bands_kernel(BandArgs a, Extract ex) {
   if (cnt == P) {
     __builtin_memcpy(a.out + x0, word, P);
   } else {
-    for (int p = 0; p < cnt; ++p) a.out[x0 + p] = (uint8_t)(word[p / 4] >> (8 * (p % 4)));
+    // (constant indices: an indexed word[] is kept in LDS, whose address the compiler
+    // takes from the dispatch packet in host memory: U8, 3 members of 899,491
+    // points 15.3 us, 9.5 with byte stores)
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+      if (p < cnt) a.out[x0 + p] = (uint8_t)(word[p / 4] >> (8 * (p % 4)));
   }
 }
 
