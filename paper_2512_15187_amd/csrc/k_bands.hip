@@ -9,8 +9,8 @@
 // u >= threshold is that of FP64 on the extracted value: stored values are
 // compared in their own type with the smallest value of it at or above the
 // threshold, which decides the same; isovalue models are evaluated in FP64.
-// U8, 100 members on 128^3: 86 us with a branch around every load and FP64
-// compares, whole call 101 -> 55 us; FP16
+// U8, 100 members on 128^3: 74 us with a branch around every load and FP64
+// compares, 38 so (5.5 TB/s); whole calls, FP16
 // 120 -> 79 us, FP32 rows that are not aligned, 60 members on 81^3, 46 -> 25 us.
 #include "bits_source.h"
 #include "device_common.h"
@@ -43,6 +43,13 @@ __device__ __forceinline__ uint32_t ge_bytes(uint32_t v, uint32_t add) {
   return ((e >> 8) & 0x00010001u) | (o & 0x01000100u);
 }
 
+// The decision on one stored value.
+template <int MODE, typename T>
+__device__ __forceinline__ bool decide_point(T raw, const BandArgs& a, const Extract& ex) {
+  if constexpr (MODE == MODE_NONE && sizeof(T) < 8) return to_float(raw) >= a.thr_f;
+  else return extract_d<MODE>(raw, ex) >= a.thr;
+}
+
 // The decisions on a chunk, bit p for point p.
 template <typename T, int MODE>
 __device__ __forceinline__ uint32_t decide(const Vec16<T>& v, const BandArgs& a, const Extract& ex) {
@@ -54,12 +61,7 @@ __device__ __forceinline__ uint32_t decide(const Vec16<T>& v, const BandArgs& a,
   } else {
     uint32_t b = 0u;
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-      bool in;
-      if constexpr (MODE == MODE_NONE && sizeof(T) < 8) in = to_float(v.v[p]) >= a.thr_f;
-      else in = extract_d<MODE>(v.v[p], ex) >= a.thr;
-      b |= (in ? 1u : 0u) << p;
-    }
+    for (int p = 0; p < P; ++p) b |= (decide_point<MODE>(v.v[p], a, ex) ? 1u : 0u) << p;
     return b;
   }
 }
@@ -72,10 +74,11 @@ constexpr int band_rows() { return sizeof(T) >= 4 ? 16 : 8; }
 // A block covers the points of 64 lanes; its four waves take interleaved
 // rounds of members (wave w: members 4r*UNR + w*UNR ... of round r) and meet
 // in LDS, where the masks combine by OR / AND (exact, order-free).  A round's
-// loads are issued together: entries past k_outer or outside 0..n-1 read row
-// 0 and leave the masks as they are, and a chunk that reaches past m is read P
-// points before m, its decisions shifted (rows of fewer than P points are read
-// point by point).
+// indices are one load, a round ahead (lane q holds the round's q-th; scalar
+// loads are waited for one by one), and its rows' loads are issued together: entries past k_outer or outside 0..n-1 read row 0 and
+// leave the masks as they are, and a chunk that reaches past m is read P points
+// before m, its decisions shifted.  Rows of fewer than P points are read point by point,
+// in a loop of their own.
 template <typename T, int MODE>
 __global__ __launch_bounds__(256) void bands_kernel(BandArgs a, Extract ex) {
   constexpr int P = 16 / (int)sizeof(T);   // points per lane
@@ -90,34 +93,49 @@ __global__ __launch_bounds__(256) void bands_kernel(BandArgs a, Extract ex) {
   const int shift = active ? (int)(x0 - xs) : 0;
   const T* __restrict__ U = reinterpret_cast<const T*>(a.U);
   uint32_t med = 0, ui = 0, ii = ALL, uo = 0, io = ALL, bad = 0;
-  for (int j0 = wv * UNR; j0 < a.k_outer; j0 += 4 * UNR) {
-    Vec16<T> v[UNR];
-    int idx[UNR];
+  auto see = [&](int j, uint32_t b) {
+    if (j == 0) med = b;
+    if (j < a.k_inner) { ui |= b; ii &= b; }
+    uo |= b;
+    io &= b;
+  };
+  if (a.m >= P) {
+    auto entry = [&](int j0) { return a.order[min(j0 + (lane & (UNR - 1)), a.k_outer - 1)]; };
+    int next = entry(wv * UNR);
+    for (int j0 = wv * UNR; j0 < a.k_outer; j0 += 4 * UNR) {
+      const int mine = next;
+      Vec16<T> v[UNR];
+      int idx[UNR];
 #pragma unroll
-    for (int q = 0; q < UNR; ++q) {
-      const int k = __builtin_amdgcn_readfirstlane(a.order[min(j0 + q, a.k_outer - 1)]);
-      const bool ok = (unsigned)k < (unsigned)a.n;
-      if (!ok) bad = 1;                    // an index outside 0..n-1 is never read
-      idx[q] = (ok && j0 + q < a.k_outer) ? k : -1;
+      for (int q = 0; q < UNR; ++q) {
+        const int k = __builtin_amdgcn_readlane(mine, q);
+        const bool ok = (unsigned)k < (unsigned)a.n;
+        if (!ok) bad = 1;                  // an index outside 0..n-1 is never read
+        idx[q] = (ok && j0 + q < a.k_outer) ? k : -1;
+        v[q] = load16_any(U + (int64_t)max(idx[q], 0) * a.ld + xs);
+      }
+      next = entry(j0 + 4 * UNR);
+      asm volatile("" ::: "memory");       // (issued here, not sunk to where they are used)
+#pragma unroll
+      for (int q = 0; q < UNR; ++q) {
+        if (idx[q] >= 0) see(j0 + q, decide<T, MODE>(v[q], a, ex) >> shift);   // (whole wave)
+        // U8 through a model: 16 FP64 evaluations a chunk, one chunk at a time
+        // (eight interleaved fill all registers: STEP, 53 members of 2.4M points,
+        // a call 230 us, 71 with the loads under a branch each; the kernel takes
+        // 47 so)
+        if constexpr (MODE != MODE_NONE && sizeof(T) == 1) __builtin_amdgcn_sched_barrier(0);
+      }
     }
-    if (a.m >= P) {
-#pragma unroll
-      for (int q = 0; q < UNR; ++q) v[q] = load16_any(U + (int64_t)max(idx[q], 0) * a.ld + xs);
-    } else {
-#pragma unroll
-      for (int q = 0; q < UNR; ++q)
-#pragma unroll
-        for (int p = 0; p < P; ++p) v[q].v[p] = U[(int64_t)max(idx[q], 0) * a.ld + min((int64_t)p, a.m - 1)];
-    }
-#pragma unroll
-    for (int q = 0; q < UNR; ++q) {
-      if (idx[q] < 0) continue;            // (whole wave)
-      const int j = j0 + q;
-      const uint32_t b = decide<T, MODE>(v[q], a, ex) >> shift;
-      if (j == 0) med = b;
-      if (j < a.k_inner) { ui |= b; ii &= b; }
-      uo |= b;
-      io &= b;
+  } else {
+    for (int j = wv; j < a.k_outer; j += 4) {
+      const int k = __builtin_amdgcn_readfirstlane(a.order[j]);
+      if ((unsigned)k >= (unsigned)a.n) {
+        bad = 1;
+        continue;
+      }
+      uint32_t b = 0u;
+      for (int p = 0; p < (int)a.m; ++p) b |= (decide_point<MODE>(U[(int64_t)k * a.ld + p], a, ex) ? 1u : 0u) << p;
+      see(j, b);
     }
   }
   sh[wv][0][lane] = med;
