@@ -117,12 +117,10 @@ struct SrcValues {
 #pragma unroll
     for (int k = 0; k < L; ++k) b[0] |= bits(r.v[k], ex) << (P * k);
   }
-  // The ragged last tile where the order of a tile's points does not matter
-  // (they meet only the same points of the other members): the blocks of
-  // load(), those that reach past m read P points before m and shifted.  Needs
-  // m >= P, so that no load sits under a branch: with load_tail() the
-  // single-pass kernel waited for each member's loads in turn (n = 33 FP32 on
-  // 90^3, thresholded: 53 us, 38 so; 42 in two passes).
+  // The ragged last tile: the blocks of load(), those that reach past m read P
+  // points before m and shifted.  Needs m >= P, so that no load sits under a
+  // branch: with one the single-pass kernel waited for each member's loads in turn
+  // (n = 33 FP32 on 90^3, thresholded: 53 us, 38 so; 42 in two passes).
   typedef Raw EdgeRaw;
   __device__ __forceinline__ EdgeRaw load_edge(const T* row, int64_t tile, int64_t m, int lane) const {
     EdgeRaw r;
@@ -130,44 +128,56 @@ struct SrcValues {
     for (int k = 0; k < L; ++k) r.v[k] = load16u(row + min(tile * TILE + (64 * k + lane) * P, m - P));
     return r;
   }
+  // Its words: where the order of a tile's points does not matter (they meet only
+  // the same points of the other members) ...
   __device__ __forceinline__ void words_edge(const EdgeRaw& r, int64_t tile, int64_t m, int lane, const Extract& ex,
                                              uint32_t (&b)[1]) const {
     b[0] = 0u;
 #pragma unroll
-    for (int k = 0; k < L; ++k) {
-      const int left = (int)max((int64_t)0, min((int64_t)P, m - (tile * TILE + (64 * k + lane) * P)));
-      const uint32_t w = left > 0 ? (bits(r.v[k], ex) >> (P - left)) & ((1u << left) - 1u) : 0u;
-      b[0] |= w << (P * k);
-    }
+    for (int k = 0; k < L; ++k) b[0] |= edge_bits(r, k, tile, m, lane, ex) << (P * k);
   }
-  // The ragged last tile in the order of the points: the lane's word holds the
-  // 32 points from tile * TILE + 32 lane.  A block that reaches past m is read P points before
-  // m and its bits shifted, so that no load sits under a branch of its own
-  // (rows of fewer than P points are read point by point).
-  __device__ __forceinline__ Raw load_tail(const T* row, int64_t tile, int64_t m, int lane) const {
-    Raw r;
-    if (m >= P) {
+  // ... and in the order of the points, lane l's word holding the 32 points from
+  // tile * TILE + 32 l (called by the whole wave).  Word w is the blocks of L
+  // neighbouring lanes of one load: they meet by lane moves, the j-th of such lanes
+  // keeps the word of the j-th load, and the words change places.  (Loaded in this
+  // order, L blocks of 16 bytes from 32 points per lane, every load of the wave touches
+  // 64 lines: FP64, n = 1,000 on 65,488 points, whole call 160 us, 138 so.)
+  __device__ __forceinline__ void words_tail(const EdgeRaw& r, int64_t tile, int64_t m, int lane, const Extract& ex,
+                                             uint32_t (&b)[1]) const {
+    const int j = lane % L;
+    uint32_t own = 0u;
 #pragma unroll
-      for (int k = 0; k < L; ++k) r.v[k] = load16u(row + min(tile * TILE + (int64_t)lane * 32 + k * P, m - P));
-    } else {
-#pragma unroll
-      for (int k = 0; k < L; ++k) r.v[k] = Vec16<T>{};
-#pragma unroll
-      for (int p = 0; p < P; ++p) r.v[0].v[p] = row[min((int64_t)p, m - 1)];
+    for (int k = 0; k < L; ++k) {
+      int e = (int)(edge_bits(r, k, tile, m, lane, ex) << (P * j));
+      e |= __builtin_amdgcn_update_dpp(0, e, 0xB1, 0xF, 0xF, false);                          // quad_perm [1,0,3,2]
+      if constexpr (L > 2) e |= __builtin_amdgcn_update_dpp(0, e, 0x4E, 0xF, 0xF, false);     // quad_perm [2,3,0,1]
+      if constexpr (L > 4) e |= __builtin_amdgcn_update_dpp(0, e, 0x141, 0xF, 0xF, false);    // row_half_mirror
+      if constexpr (L > 8) e |= __builtin_amdgcn_update_dpp(0, e, 0x140, 0xF, 0xF, false);    // row_mirror
+      own = j == k ? (uint32_t)e : own;
     }
+    b[0] = (uint32_t)__shfl((int)own, (lane % (2 * P)) * L + lane / (2 * P), 64);
+  }
+  // Rows of fewer than P points, read point by point: the first block of lane 0.
+  // (A form of its own: where one function chose between this and vector loads,
+  // the compiler merged them into byte loads, and the ragged tile of n = 3,314 U8
+  // masks of 65,293 points took 190 of 250 us.)
+  __device__ __forceinline__ EdgeRaw load_short(const T* row, int64_t m) const {
+    EdgeRaw r{};
+#pragma unroll
+    for (int p = 0; p < P; ++p) r.v[0].v[p] = row[min((int64_t)p, m - 1)];
     return r;
   }
-  __device__ __forceinline__ void words_tail(const Raw& r, int64_t tile, int64_t m, int lane, const Extract& ex,
-                                             uint32_t (&b)[1]) const {
-    b[0] = 0u;
-#pragma unroll
-    for (int k = 0; k < L; ++k) {
-      const int64_t x = tile * TILE + (int64_t)lane * 32 + k * P;
-      const int left = (int)max((int64_t)0, min((int64_t)P, m - x));   // points of the block below m
-      const int sh = (m >= P) ? P - left : 0;
-      const uint32_t w = left > 0 ? (bits(r.v[k], ex) >> sh) & ((1u << left) - 1u) : 0u;
-      b[0] |= w << (P * k);
-    }
+  __device__ __forceinline__ void words_short(const EdgeRaw& r, int64_t m, int lane, const Extract& ex,
+                                              uint32_t (&b)[1]) const {
+    b[0] = lane == 0 ? bits(r.v[0], ex) & ((1u << (int)m) - 1u) : 0u;
+  }
+
+ private:
+  // The bits of the k-th block of load_edge(), zeros past m.
+  static __device__ __forceinline__ uint32_t edge_bits(const EdgeRaw& r, int k, int64_t tile, int64_t m, int lane,
+                                                       const Extract& ex) {
+    const int left = (int)max((int64_t)0, min((int64_t)P, m - (tile * TILE + (64 * k + lane) * P)));
+    return left > 0 ? (bits(r.v[k], ex) >> (P - left)) & ((1u << left) - 1u) : 0u;
   }
 };
 
@@ -193,17 +203,6 @@ struct SrcBytes : SrcValues<uint8_t, false> {
     const uint32_t lo = (((uint32_t)hA >> r.sh) | (nA << (16 - r.sh))) & 0xffffu;
     const uint32_t hi = ((uint32_t)hB >> r.sh) | (nB << (16 - r.sh));
     b[0] = lo | (hi << 16);
-  }
-  __device__ __forceinline__ Raw load_tail(const uint8_t* row, int64_t tile, int64_t m, int lane) const {
-    const SrcValues<uint8_t, false>::Raw t = SrcValues<uint8_t, false>::load_tail(row, tile, m, lane);
-    return Raw{__builtin_bit_cast(uint4, t.v[0]), __builtin_bit_cast(uint4, t.v[1]), uint4{}, 0};
-  }
-  __device__ __forceinline__ void words_tail(const Raw& r, int64_t tile, int64_t m, int lane, const Extract& ex,
-                                             uint32_t (&b)[1]) const {
-    SrcValues<uint8_t, false>::Raw t;
-    t.v[0] = __builtin_bit_cast(Vec16<uint8_t>, r.a);
-    t.v[1] = __builtin_bit_cast(Vec16<uint8_t>, r.b);
-    SrcValues<uint8_t, false>::words_tail(t, tile, m, lane, ex, b);
   }
 };
 inline bool bytes_misaligned(const pid_ensemble& e) {

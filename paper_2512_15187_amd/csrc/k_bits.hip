@@ -183,8 +183,10 @@ __global__ __launch_bounds__(256) void count_pack_kernel(const typename Src::Ele
   uint32_t P[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) P[k] = 0u;
-  auto rows = [&](auto fc) {
-    constexpr bool FULL = decltype(fc)::value;
+  // how: 0 the chunk lies inside the rows, 1 it is their ragged end, 2 rows of
+  // fewer points than a vector
+  auto rows = [&](auto how) {
+    constexpr int HOW = decltype(how)::value;
     for (int i = i0 + wave; i < i1; i += 32) {   // rows i, i + 4, ..., i + 28
       // (rows past the group re-read its last one: every load of the batch is
       // issued before the first is waited for)
@@ -196,18 +198,20 @@ __global__ __launch_bounds__(256) void count_pack_kernel(const typename Src::Ele
           for (int q = 0; q < FB; ++q) b[q0 + q] = 0u;
           continue;
         }
-        typename Src::Raw raw[FB];
+        typename std::conditional<HOW == 0, typename Src::Raw, typename Src::EdgeRaw>::type raw[FB];
 #pragma unroll
         for (int q = 0; q < FB; ++q) {
           const typename Src::Elem* row = U + (int64_t)min(i + 4 * (q0 + q), i1 - 1) * ld;
-          if constexpr (FULL) raw[q] = src.load(row, c, lane);
-          else raw[q] = src.load_tail(row, c, m, lane);
+          if constexpr (HOW == 0) raw[q] = src.load(row, c, lane);
+          else if constexpr (HOW == 1) raw[q] = src.load_edge(row, c, m, lane);
+          else raw[q] = src.load_short(row, m);
         }
 #pragma unroll
         for (int q = 0; q < FB; ++q) {
           uint32_t w[1];
-          if constexpr (FULL) src.words(raw[q], ex, w);
-          else src.words_tail(raw[q], c, m, lane, ex, w);
+          if constexpr (HOW == 0) src.words(raw[q], ex, w);
+          else if constexpr (HOW == 1) src.words_tail(raw[q], c, m, lane, ex, w);
+          else src.words_short(raw[q], m, lane, ex, w);
           const bool in = i + 4 * (q0 + q) < i1;   // (whole wave)
           b[q0 + q] = in ? w[0] : 0u;
           if (in && wi < W) pk[(int64_t)(i + 4 * (q0 + q)) * Wp + wi] = w[0];
@@ -218,8 +222,9 @@ __global__ __launch_bounds__(256) void count_pack_kernel(const typename Src::Ele
       add4(P, cnt);
     }
   };
-  if (m - c * 2048 >= 2048) rows(std::true_type());
-  else rows(std::false_type());
+  if (m - c * 2048 >= 2048) rows(std::integral_constant<int, 0>());
+  else if (m >= Src::P) rows(std::integral_constant<int, 1>());
+  else rows(std::integral_constant<int, 2>());
   if (wave > 0) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) red[wave - 1][k][lane] = P[k];

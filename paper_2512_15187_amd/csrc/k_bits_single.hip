@@ -34,7 +34,8 @@ constexpr int kWavePlanes = 4;  // planes of a count of up to kRows
 
 // Where a lane's words come from.  load() issues the loads of one member's
 // words of a tile that lies inside the row; words() turns them into bits;
-// load_tail() and words_tail() do it for the ragged last tile.  Which point sits in which
+// load_edge() and words_edge() do it for the ragged last tile, load_short() and
+// words_short() for rows of fewer than P points.  Which point sits in which
 // bit is the same for every member, and nothing else depends on it.  (Stored
 // values: SrcValues in bits_source.h.)
 
@@ -59,20 +60,15 @@ struct SrcBits {
 #pragma unroll
     for (int q = 0; q < V; ++q) b[q] = r.w[q];
   }
-  // (the ragged last tile; load_edge and load_tail are the same here)
+  // (the ragged last tile)
   static constexpr int P = 1;
   __device__ __forceinline__ Raw load_edge(const uint32_t* row, int64_t tile, int64_t m, int lane) const {
-    return load_tail(row, tile, m, lane);
-  }
-  template <typename... A>
-  __device__ __forceinline__ void words_edge(A&&... a) const { words_tail(a...); }
-  __device__ __forceinline__ Raw load_tail(const uint32_t* row, int64_t tile, int64_t m, int lane) const {
     Raw r;
 #pragma unroll
     for (int q = 0; q < V; ++q) r.w[q] = row[min((tile * 64 + lane) * V + q, (m + 31) / 32 - 1)];
     return r;
   }
-  __device__ __forceinline__ void words_tail(const Raw& r, int64_t tile, int64_t m, int lane, const Extract&,
+  __device__ __forceinline__ void words_edge(const Raw& r, int64_t tile, int64_t m, int lane, const Extract&,
                                              uint32_t (&b)[V]) const {
     const int64_t W = (m + 31) / 32;
 #pragma unroll
@@ -173,7 +169,7 @@ __global__ __launch_bounds__(64 * NWMAX) void bits_single_kernel(const typename 
 
   // BATCH members' loads are issued together; rows past n re-read row n - 1
   // and count as empty
-  // how: 0 a whole tile, 1 the ragged last one, 2 the same with Src's edge loads
+  // how: 0 a whole tile, 1 the ragged last one, 2 that of rows of fewer than P points
   auto tile_step = [&](int64_t tile, auto how) {
     constexpr int HOW = decltype(how)::value;
     uint32_t b[kRows][V];
@@ -181,12 +177,12 @@ __global__ __launch_bounds__(64 * NWMAX) void bits_single_kernel(const typename 
     for (int r0 = 0; r0 < kRows; r0 += Src::BATCH) {
       if (r0 < nr) {
         auto batch = [&](auto load, auto words) {
-          decltype(load(rows)) raw[Src::BATCH];
+          decltype(load(src, rows)) raw[Src::BATCH];
 #pragma unroll
-          for (int q = 0; q < Src::BATCH; ++q) raw[q] = load(rows + (int64_t)min(r0 + q, nr - 1) * ld);
+          for (int q = 0; q < Src::BATCH; ++q) raw[q] = load(src, rows + (int64_t)min(r0 + q, nr - 1) * ld);
 #pragma unroll
           for (int q = 0; q < Src::BATCH; ++q) {
-            words(raw[q], b[r0 + q]);
+            words(src, raw[q], b[r0 + q]);
             const uint32_t keep = r0 + q < nr ? 0xffffffffu : 0u;
 #pragma unroll
             for (int v = 0; v < V; ++v) b[r0 + q][v] &= keep;
@@ -194,13 +190,14 @@ __global__ __launch_bounds__(64 * NWMAX) void bits_single_kernel(const typename 
         };
         typedef const typename Src::Elem* Row;
         if constexpr (HOW == 0)
-          batch([&](Row p) { return src.load(p, tile, lane); }, [&](const auto& x, auto& w) { src.words(x, ex, w); });
+          batch([&](const auto& s, Row p) { return s.load(p, tile, lane); },
+                [&](const auto& s, const auto& x, auto& w) { s.words(x, ex, w); });
         else if constexpr (HOW == 1)
-          batch([&](Row p) { return src.load_tail(p, tile, m, lane); },
-                [&](const auto& x, auto& w) { src.words_tail(x, tile, m, lane, ex, w); });
+          batch([&](const auto& s, Row p) { return s.load_edge(p, tile, m, lane); },
+                [&](const auto& s, const auto& x, auto& w) { s.words_edge(x, tile, m, lane, ex, w); });
         else
-          batch([&](Row p) { return src.load_edge(p, tile, m, lane); },
-                [&](const auto& x, auto& w) { src.words_edge(x, tile, m, lane, ex, w); });
+          batch([&](const auto& s, Row p) { return s.load_short(p, m); },
+                [&](const auto& s, const auto& x, auto& w) { s.words_short(x, m, lane, ex, w); });
       } else {
 #pragma unroll
         for (int q = 0; q < Src::BATCH; ++q)
@@ -212,8 +209,9 @@ __global__ __launch_bounds__(64 * NWMAX) void bits_single_kernel(const typename 
   };
   for (int64_t tile = blockIdx.x; tile < nfull; tile += gridDim.x) tile_step(tile, std::integral_constant<int, 0>());
   if (nfull < ntiles && blockIdx.x == (unsigned)(nfull % gridDim.x)) {
-    if (Src::P == 1 || m >= Src::P) tile_step(nfull, std::integral_constant<int, 2>());
-    else tile_step(nfull, std::integral_constant<int, 1>());
+    if constexpr (Src::P == 1) tile_step(nfull, std::integral_constant<int, 1>());
+    else if (m >= Src::P) tile_step(nfull, std::integral_constant<int, 1>());
+    else tile_step(nfull, std::integral_constant<int, 2>());
   }
   const int nblk = gridDim.x;
 #pragma unroll
