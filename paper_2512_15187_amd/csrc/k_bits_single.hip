@@ -235,8 +235,12 @@ hipError_t launch_src(const pid_ensemble& e, int64_t ld, const Extract& ex, cons
   // Workgroups: about 8 waves per CU (14 with 4 words per lane), each streaming
   // its share of the tiles; more streams are slower (U8, N = 50 on 256^3: 175,
   // 180, 191 and 236 us with 7, 14, 28 and 112 waves per CU; packed on 352^3:
-  // 108, 76, 82 and 106 us).
-  const int64_t fit = (int64_t)device_cu_count() * std::max(1, (Src::V == 4 ? 14 : 8) / nw);
+  // 108, 76, 82 and 106 us).  Thresholded 16-bit fields 16: they compare twice
+  // the points a byte as FP32 (N = 33 on 3,673,760 points 87, 65 and 55 us with 5,
+  // 10 and 15 waves per CU, 74 in two passes; N = 44 106, 81 with 6 and 12, 98 in
+  // two passes).
+  const int waves = Src::V == 4 ? 14 : (sizeof(typename Src::Elem) == 2 ? 16 : 8);
+  const int64_t fit = (int64_t)device_cu_count() * std::max(1, waves / nw);
   *nblk = (int)std::min(ntiles, std::min(max_blocks, std::max(fit, (ntiles + 8000) / 8001)));
   const typename Src::Elem* U = reinterpret_cast<const typename Src::Elem*>(e.data);
   const dim3 block(64 * nw);
