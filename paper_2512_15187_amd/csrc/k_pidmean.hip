@@ -55,8 +55,16 @@ __device__ __forceinline__ CT extract_ct(T raw, const Extract& e) {
 // raw 16-byte vectors in registers and widen them again in the second phase;
 // fields keep the extracted probabilities.
 // part layout: [2][n][grid.x] doubles (m, then A).
+// Waves per SIMD that the registers have to allow: the row pass of thresholded
+// fields would take 134 to 143 (three waves instead of four: FP32, n = 200 on
+// 100,096 weighted points 59 -> 67 us).
+template <typename T, int MODE, int MPW, bool SFROM>
+constexpr int soft_waves() {
+  return SFROM && MODE == MODE_STEP && (sizeof(T) == 4 || (sizeof(T) == 2 && MPW <= 8)) ? 4 : 1;
+}
+
 template <typename T, int MODE, int MPW, bool WEIGHTED, bool SFROM, int NWMAX>
-__global__ __launch_bounds__(64 * NWMAX) void pidmean_soft_kernel(
+__global__ __launch_bounds__(64 * NWMAX, (soft_waves<T, MODE, MPW, SFROM>())) void pidmean_soft_kernel(
     const T* __restrict__ U, int64_t ld, int n, int64_t m, const float* __restrict__ w,
     Extract ex, int64_t ntiles, const void* __restrict__ sglob, double* __restrict__ part) {
   using CT = ComputeT<T>;
@@ -75,9 +83,11 @@ __global__ __launch_bounds__(64 * NWMAX) void pidmean_soft_kernel(
   for (int r = 0; r < MPW; ++r) { accm[r] = CT(0); acca[r] = CT(0); }
 
   int it = 0;
-  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x, ++it) {
+  // WHOLE: the tile lies inside the rows
+  auto step = [&](int64_t tile, auto whole) {
+    constexpr bool WHOLE = decltype(whole)::value;
     const int64_t x0 = tile * TP + (int64_t)lane * PPL;
-    const bool full = (x0 + PPL <= m);
+    const bool full = WHOLE || (x0 + PPL <= m);
     // Every member's load is unconditional, so that they are all in flight
     // together (a load under a branch of its own is waited for before the
     // next one is issued); rows past n re-read row n - 1 and stay out of
@@ -85,11 +95,15 @@ __global__ __launch_bounds__(64 * NWMAX) void pidmean_soft_kernel(
     // shifted (rows shorter than a vector take guarded loads).  With element
     // loads where rows are not 16-byte aligned, PID-mean of FP16 n = 64 on
     // 201^3 took 502 us; now 211 (4.9 TB/s).
-    const bool fast = (tile + 1) * TP <= m;
+    const bool fast = WHOLE || (tile + 1) * TP <= m;
+    // (Up to 32 FP64 members not non-temporal: tiles of unaligned rows share lines.
+    // mean_weighted of n = 13 on rows of 3,644,944 points, 8-byte aligned, 168 -> 155
+    // us; of n = 40 on 1,000,000 aligned points 112 -> 120.)
+    auto load = [](const T* row) { return sizeof(T) == 8 && MPW == 4 ? load16_any(row) : load16_nt_any(row); };
     Vec16<T> vv[MPW];
     if (fast) {
 #pragma unroll
-      for (int r = 0; r < MPW; ++r) vv[r] = load16_nt_any(U + (int64_t)min(mbase + r, n - 1) * ld + x0);
+      for (int r = 0; r < MPW; ++r) vv[r] = load(U + (int64_t)min(mbase + r, n - 1) * ld + x0);
     } else if (m >= PPL) {
       const TailLoad<T> tail(x0, m);
 #pragma unroll
@@ -193,6 +207,60 @@ __global__ __launch_bounds__(64 * NWMAX) void pidmean_soft_kernel(
       }
       accm[r] += tm;
       acca[r] += ta;
+    }
+    ++it;
+  };
+  if constexpr (!SFROM || sizeof(T) == 1) {
+    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) step(tile, std::false_type());
+  } else {
+    const int64_t nfull = m / TP;
+    for (int64_t tile = blockIdx.x; tile < nfull; tile += gridDim.x) step(tile, std::true_type());
+    // The ragged tile (the last of its workgroup), two members at a time: no sums
+    // meet here, so nothing else has to stay in registers.  (In one body with the
+    // whole tiles its loads and shifts are the kernel's registers, and the loaded
+    // values, coming from two branches, are copied as they arrive: the weighted
+    // FP32 row pass took 129, three waves per SIMD, mean_weighted of n = 33 on 3.5M
+    // points 204 us; 190 so.)
+    constexpr int NQ = 2;
+    auto ragged = [&](auto shortc) {
+      const int64_t x0 = nfull * TP + (int64_t)lane * PPL;
+      const CT* sg = reinterpret_cast<const CT*>(sglob);
+      CT s[PPL], wv[PPL];
+#pragma unroll
+      for (int p = 0; p < PPL; ++p) {
+        const int64_t x = min(x0 + p, m - 1);
+        const CT ts = sg[x], tw = WEIGHTED ? CT(w[x]) : CT(1);
+        wv[p] = (x0 + p < m) ? tw : CT(0);
+        s[p] = (x0 + p < m) ? (WEIGHTED ? ts * tw : ts) : CT(0);
+      }
+#pragma unroll
+      for (int r0 = 0; r0 < MPW; r0 += NQ) {
+        Vec16<T> v[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+          const T* row = U + (int64_t)min(mbase + r0 + q, n - 1) * ld;
+          if constexpr (decltype(shortc)::value) v[q] = load16_guarded(row, x0, m);
+          else v[q] = TailLoad<T>(x0, m)(row);
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+          CT tm = CT(0), ta = CT(0);
+#pragma unroll
+          for (int p = 0; p < PPL; ++p) {
+            CT uv = extract_ct<MODE, T, CT>(v[q].v[p], ex);
+            if constexpr (!KEEP_RAW) uv = (x0 + p < m) ? uv : CT(0);
+            tm += WEIGHTED ? wv[p] * uv : uv;
+            ta += s[p] * uv;
+          }
+          accm[r0 + q] += tm;
+          acca[r0 + q] += ta;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    if (nfull < ntiles && blockIdx.x == (unsigned)(nfull % gridDim.x)) {
+      if (m >= PPL) ragged(std::false_type());
+      else ragged(std::true_type());   // (rows shorter than a vector)
     }
   }
 
@@ -605,22 +673,28 @@ __global__ __launch_bounds__(256) void colsum_part_kernel(const T* __restrict__ 
     }
   };
   // vector loads of four rows in flight, at any row address; the ragged last
-  // tile's are shifted (rows shorter than a vector take element loads)
-  auto sum = [&](auto load) {
+  // tile's are shifted, and rows shorter than a vector take element loads, one row
+  // at a time (with four, their registers are the kernel's: 16-bit input 49 -> 96,
+  // five waves per SIMD instead of eight)
+  auto sum = [&](auto rows, auto load) {
     int i = i0 + q;
-    for (; i + 12 < i1; i += 16) {
-      const Vec16<T> a0 = load(i), a1 = load(i + 4), a2 = load(i + 8), a3 = load(i + 12);
-      add(i, a0); add(i + 4, a1); add(i + 8, a2); add(i + 12, a3);
+    if constexpr (decltype(rows)::value == 4) {
+      for (; i + 12 < i1; i += 16) {
+        const Vec16<T> a0 = load(i), a1 = load(i + 4), a2 = load(i + 8), a3 = load(i + 12);
+        add(i, a0); add(i + 4, a1); add(i + 8, a2); add(i + 12, a3);
+      }
     }
     for (; i < i1; i += 4) add(i, load(i));
   };
+  constexpr std::integral_constant<int, 1> one;
+  constexpr std::integral_constant<int, 4> four;
   if ((int64_t)(blockIdx.x + 1) * (64 * PPL) <= m) {
-    sum([&](int i) { return load16_nt_any(U + (int64_t)i * ld + x0); });
+    sum(four, [&](int i) { return load16_nt_any(U + (int64_t)i * ld + x0); });
   } else if (m >= PPL) {
     const TailLoad<T> tail(x0, m);
-    sum([&](int i) { return tail(U + (int64_t)i * ld); });
+    sum(one, [&](int i) { return tail(U + (int64_t)i * ld); });
   } else {
-    sum([&](int i) { return load16_guarded(U + (int64_t)i * ld, x0, m); });
+    sum(one, [&](int i) { return load16_guarded(U + (int64_t)i * ld, x0, m); });
   }
 #pragma unroll
   for (int p = 0; p < PPL; ++p) part[q][lane * PPL + p] = t[p];
