@@ -173,22 +173,30 @@ __device__ __forceinline__ Vec16<T> load16_nt(const T* p) {
 }
 
 // 16 bytes from an address aligned to the element only (unaligned vector loads
-// are native here).
+// are native here).  The pointer types are named in place: as arguments or members
+// of a template they would lose their alignment, and the loads would promise the
+// compiler 16 bytes.
 typedef unsigned int u32x4_a1 __attribute__((ext_vector_type(4), aligned(1)));
 typedef unsigned int u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
 typedef unsigned int u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned int u32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));
 template <typename T>
-using U32x4Any =
-    typename std::conditional<sizeof(T) == 1, u32x4_a1, typename std::conditional<sizeof(T) == 2, u32x4_a2,
-    typename std::conditional<sizeof(T) == 4, u32x4_a4, u32x4_a8>::type>::type>::type;
-template <typename T>
 __device__ __forceinline__ Vec16<T> load16_any(const T* p) {
-  return __builtin_bit_cast(Vec16<T>, (u32x4)*reinterpret_cast<const U32x4Any<T>*>(p));
+  u32x4 r;
+  if constexpr (sizeof(T) == 1) r = *reinterpret_cast<const u32x4_a1*>(p);
+  else if constexpr (sizeof(T) == 2) r = *reinterpret_cast<const u32x4_a2*>(p);
+  else if constexpr (sizeof(T) == 4) r = *reinterpret_cast<const u32x4_a4*>(p);
+  else r = *reinterpret_cast<const u32x4_a8*>(p);
+  return __builtin_bit_cast(Vec16<T>, r);
 }
 template <typename T>
 __device__ __forceinline__ Vec16<T> load16_nt_any(const T* p) {
-  return __builtin_bit_cast(Vec16<T>, (u32x4)__builtin_nontemporal_load(reinterpret_cast<const U32x4Any<T>*>(p)));
+  u32x4 r;
+  if constexpr (sizeof(T) == 1) r = __builtin_nontemporal_load(reinterpret_cast<const u32x4_a1*>(p));
+  else if constexpr (sizeof(T) == 2) r = __builtin_nontemporal_load(reinterpret_cast<const u32x4_a2*>(p));
+  else if constexpr (sizeof(T) == 4) r = __builtin_nontemporal_load(reinterpret_cast<const u32x4_a4*>(p));
+  else r = __builtin_nontemporal_load(reinterpret_cast<const u32x4_a8*>(p));
+  return __builtin_bit_cast(Vec16<T>, r);
 }
 
 // The points x0, x0 + 1, ... of a row of m points, for the lanes of a row's
