@@ -596,11 +596,13 @@ void launch_gram_raw(const GramArgs& ga, hipStream_t st, const KernelTimer& tm) 
   // larger ends: 8 and more row blocks in a unit lose to the small units below
   // at 32 slabs a split (n = 512 on 256^2 42.1 -> 44.7 us) and win at 50
   // (on 320^2 83.8 -> 65.7), fewer are level at 8 (n = 384 on 160^2 25.7 ->
-  // 27.0; on 256^2, 21 slabs, 32.8 -> 32.0).  One unit (up to 8 row blocks)
-  // has no others to lose to, but for U8 with more splits than CUs (n = 192 on
-  // 176^3 223 -> 249 us).
-  if (cv && (cv->units > 1 ? ga.slabs >= (int64_t)(cv->maxblk >= 8 ? 48 : 12) * ga.nsplit
-                           : sizeof(Tin) == 2 || ga.nsplit <= 256)) {
+  // 27.0; on 256^2, 21 slabs, 32.8 -> 32.0).  One unit (up to 8 row blocks) has
+  // no others to lose to.  U8, this and the big units below: n = 136 on 160^3
+  // 128 and 145 us, on 216^3 267 and 300; n = 256 on 128^3 121 and 150, on
+  // 160^3 245 and 247, on 176^3 334 and 299: which is ahead from 5 row blocks on
+  // goes by the row stride (the channels its rows meet on), not by the length
+  // of the splits (at most one per CU; 64 to 308 slabs in these).
+  if (cv && (cv->units == 1 || ga.slabs >= (int64_t)(cv->maxblk >= 8 ? 48 : 12) * ga.nsplit)) {
     auto cover = [&](auto lw, auto nt, auto mc) {
       go(gram_raw_cover_kernel<Tin, MT, decltype(lw)::value, decltype(nt)::value, decltype(mc)::value>,
          cv->units * ga.nsplit, 1024, (size_t)4 * cv->maxblk * 4096, *cv);
@@ -618,7 +620,7 @@ void launch_gram_raw(const GramArgs& ga, hipStream_t st, const KernelTimer& tm) 
   // 256 CUs), else the big ones, which stage fewer rows per split: n = 1000 on
   // 256^2 386 -> 151 small and 176 big, n = 2048 on 256^2 1044 -> 405 and 385.
   const int us = raw_units(false, ga.nbt), ub = raw_units(true, ga.nbt);
-  const bool big = ga.nbt <= 8 || us * ga.nsplit > 512;
+  const bool big = us * ga.nsplit > 512;
   if (big) go(gram_raw_kernel<Tin, MT, true>, ub * ga.nsplit, 64 * RawGeom<true>::NW, RawGeom<true>::LDS, ub);
   else go(gram_raw_kernel<Tin, MT, false>, us * ga.nsplit, 64 * RawGeom<false>::NW, RawGeom<false>::LDS, us);
 }
