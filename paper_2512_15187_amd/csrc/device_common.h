@@ -160,18 +160,6 @@ struct Vec16 {
   T v[N];
 };
 
-template <typename T>
-__device__ __forceinline__ Vec16<T> load16(const T* p) {
-  uint4 r = *reinterpret_cast<const uint4*>(p);
-  return __builtin_bit_cast(Vec16<T>, r);
-}
-
-template <typename T>
-__device__ __forceinline__ Vec16<T> load16_nt(const T* p) {
-  u32x4 r = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
-  return __builtin_bit_cast(Vec16<T>, r);
-}
-
 // 16 bytes from an address aligned to the element only (unaligned vector loads
 // are native here).  The pointer types are named in place: as arguments or members
 // of a template they would lose their alignment, and the loads would promise the

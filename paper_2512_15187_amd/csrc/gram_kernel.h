@@ -247,7 +247,6 @@ __device__ __forceinline__ void mfma_slab_reuse(const unsigned char* lbuf, int P
 template <typename Tin, int MT, int MODE, int MAXT, int CPR, int CH, bool WEIGHTED>
 __global__ __launch_bounds__(512) void gram_kernel(GramArgs a) {
   using TR = MTraits<MT>;
-  using E = typename TR::E;
   constexpr int EPC = 16 / sizeof(Tin);          // elements per 16-byte chunk
   constexpr int KS = CPR * EPC;                  // points per slab
   constexpr int G4 = EPC < 4 ? EPC : 4;          // elements converted together

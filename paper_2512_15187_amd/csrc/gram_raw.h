@@ -294,7 +294,7 @@ __global__ __launch_bounds__(64 * RawGeom<BIG>::NW, 2) void gram_raw_kernel(Gram
   }
 }
 
-// One super-tile of at most RI = 64, 128 or 256 rows: SPI = 256 / RI slabs
+// One super-tile of at most RI = 64 or 128 rows: SPI = 256 / RI slabs
 // share the 32 KB of a ring slot, so that as many bytes stay in flight, and as
 // much is read between two barriers, for few rows as for many.  A wave
 // multiplies sub-tiles wave, wave + NW, ... of the triangle, slab by slab.

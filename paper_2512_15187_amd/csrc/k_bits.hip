@@ -149,8 +149,6 @@ __global__ __launch_bounds__(256) void pack_bits_kernel(const uint8_t* __restric
 }
 
 // ---------------------------------------------------------------- pass 1
-constexpr int kB1Group = 255;   // members per group of the column counts (8 planes)
-
 // Stored values (U8 0/1 masks, or fields under the sharp isovalue).  Block =
 // four waves on one chunk of 2048 points (blockIdx.x) and one member group
 // (blockIdx.y): wave q packs the group's rows q, q + 4, ... of the chunk into
@@ -648,16 +646,13 @@ hipError_t b1_rows_finalize(const B1Plan& p, const uint32_t* U, int64_t ldw, boo
     auto go = [&](auto kern) {
       hipLaunchKernelGGL(kern, grid, 256, 0, st, U, ldw, (int)n, p.W, lastmask, planes, p.Wp, ntiles, mw, part);
     };
-    auto wide = [&](auto kern) {
-      hipLaunchKernelGGL(kern, grid, 256, 0, st, U, ldw, (int)n, p.W, lastmask, planes, p.Wp, ntiles, mw, part);
-    };
     switch (p.kt) {
       case 8: v == 4 ? go(b1_rows_kernel<8, 4>) : go(b1_rows_kernel<8, 1>); break;
       case 10: v == 4 ? go(b1_rows_kernel<10, 4>) : go(b1_rows_kernel<10, 1>); break;
       case 12: v == 4 ? go(b1_rows_kernel<12, 4>) : go(b1_rows_kernel<12, 1>); break;
       case 14: v == 4 ? go(b1_rows_kernel<14, 4>) : go(b1_rows_kernel<14, 1>); break;
       case 16: v == 4 ? go(b1_rows_kernel<16, 4>) : go(b1_rows_kernel<16, 1>); break;
-      default: v == 2 ? wide(b1_rows_wide_kernel<2>) : wide(b1_rows_wide_kernel<1>); break;
+      default: v == 2 ? go(b1_rows_wide_kernel<2>) : go(b1_rows_wide_kernel<1>); break;
     }
   }
   return b1_finalize(part, ntiles, n, red, out, st);

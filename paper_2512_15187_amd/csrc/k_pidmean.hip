@@ -1342,9 +1342,6 @@ hipError_t launch_pairs_linear(const pid_ensemble& e, int iso_kind, const Extrac
   else
     hipLaunchKernelGGL(inv_mass_kernel<float>, (int)((e.n + 255) / 256), 256, 0, st, mass, (int)e.n, (float*)coef);
   // passes 2 and 3: t, then B
-  const int eb = elem_bytes_of(e.dtype);
-  const bool vec = ((reinterpret_cast<uintptr_t>(e.data) & 15) == 0) && ((e.ld * eb) % 16 == 0) &&
-                   (e.weights == nullptr || (reinterpret_cast<uintptr_t>(e.weights) & 15) == 0);
   switch (e.dtype) {
     case PID_F64: launch_linear_t<double>(e, iso_kind, ex, p3, coef, tg, tpart, tbuf, part, st); break;
     case PID_F32: launch_linear_t<float>(e, iso_kind, ex, p3, coef, tg, tpart, tbuf, part, st); break;
@@ -1445,9 +1442,6 @@ hipError_t launch_pid_mean_weighted(const pid_ensemble& e, int iso_kind, const E
   if (e.dtype == PID_F64) hipLaunchKernelGGL(member_coef_kernel<double>, cg, 256, 0, st, member_w, (int)e.n, (double*)coef);
   else hipLaunchKernelGGL(member_coef_kernel<float>, cg, 256, 0, st, member_w, (int)e.n, (float*)coef);
   Extract ex = __builtin_bit_cast(Extract, exh);
-  const int eb = elem_bytes_of(e.dtype);
-  const bool vec = ((reinterpret_cast<uintptr_t>(e.data) & 15) == 0) && ((e.ld * eb) % 16 == 0) &&
-                   (e.weights == nullptr || (reinterpret_cast<uintptr_t>(e.weights) & 15) == 0);
   switch (e.dtype) {
     case PID_F64: launch_weighted_t<double>(e, iso_kind, ex, p3, coef, tg, tpart, sbuf, part, st); break;
     case PID_F32: launch_weighted_t<float>(e, iso_kind, ex, p3, coef, tg, tpart, sbuf, part, st); break;
