@@ -1125,13 +1125,18 @@ bool launch_gram_dma(const GramArgs& ga0, int maxt, int rows, int grid, hipStrea
     static_assert(NB >= 2, "LDS ring");
     (void)maxt;
     ga.slabs = (ga0.m * eb + 127) / 128;   // 128-byte slabs of every row
-    // launch with or without point weights (INT8 runs are unweighted: its
-    // "weighted" kernel is the unweighted one, never launched as such)
-    constexpr bool WW = MT != MT_I8;
-    auto go_w = [&](auto kw, auto k, size_t lds, int threads) {
-      if constexpr (MT == MT_I8) go(k, lds, threads);
-      else if (w) go(kw, lds, threads);
-      else go(k, lds, threads);
+    // launch with or without point weights: INT8 runs have none, and without
+    // them some calls never come here (values multiplied as they are, RAW; the
+    // piecewise-linear models on FP32 values up to 5 row blocks, REG)
+    constexpr bool RAW = MODE == MODE_NONE && raw_operand<Tin, MT>();
+    constexpr bool REG = MODE == MODE_MODEL && std::is_same<Tin, float>::value && MT == MT_F16;
+    constexpr auto yes = std::true_type();
+    constexpr auto no = std::false_type();
+    auto go_w = [&](auto kern, auto only_w, size_t lds, int threads) {
+      if constexpr (MT == MT_I8) go(kern(no), lds, threads);
+      else if constexpr (decltype(only_w)::value) go(kern(yes), lds, threads);
+      else if (w) go(kern(yes), lds, threads);
+      else go(kern(no), lds, threads);
     };
     if constexpr (MODE == MODE_GAUSS && sizeof(Tin) == 4 && MT != MT_BF16X3) {
       // the Gaussian model on FP32 values, at most 128 rows: 8 waves and
@@ -1141,8 +1146,8 @@ bool launch_gram_dma(const GramArgs& ga0, int maxt, int rows, int grid, hipStrea
       // registers that this needs.)
       if (rows <= 128) {
         const size_t lds = gram_dma_lds<Tin, MT, NT, 128>(rows, w);
-        go_w(gram_dma_kernel<Tin, MT, MODE, 3, WW, NB, NT, 8, false, 128>,
-             gram_dma_kernel<Tin, MT, MODE, 3, false, NB, NT, 8, false, 128>, lds, 512);
+        go_w([](auto wc) { return gram_dma_kernel<Tin, MT, MODE, 3, decltype(wc)::value, NB, NT, 8, false, 128>; },
+             no, lds, 512);
         return true;
       }
     }
@@ -1156,8 +1161,8 @@ bool launch_gram_dma(const GramArgs& ga0, int maxt, int rows, int grid, hipStrea
         static_assert(NB2 >= 3, "LDS ring");
         ga.slabs = (ga0.m * eb + 255) / 256;
         const size_t lds = gram_dma_lds<Tin, MT, NT, 256>(rows, w);
-        go_w(gram_dma_kernel<Tin, MT, MODE, 3, WW, NB2, NT, 16, false, 256>,
-             gram_dma_kernel<Tin, MT, MODE, 3, false, NB2, NT, 16, false, 256>, lds, 1024);
+        go_w([](auto wc) { return gram_dma_kernel<Tin, MT, MODE, 3, decltype(wc)::value, NB2, NT, 16, false, 256>; },
+             std::bool_constant<REG>(), lds, 1024);
         return true;
       }
     }
@@ -1172,12 +1177,12 @@ bool launch_gram_dma(const GramArgs& ga0, int maxt, int rows, int grid, hipStrea
       constexpr int NBG = gram_dma_nb<Tin, MT, NTG, 128>();
       static_assert(NBG >= 2, "LDS ring");
       const size_t lds = gram_dma_lds<Tin, MT, NTG, 128>(rows, w);
-      go_w(gram_dma_kernel<Tin, MT, MODE, 3, WW, NBG, NTG, 16, true, 128>,
-           gram_dma_kernel<Tin, MT, MODE, 3, false, NBG, NTG, 16, true, 128>, lds, 1024);
+      go_w([](auto wc) { return gram_dma_kernel<Tin, MT, MODE, 3, decltype(wc)::value, NBG, NTG, 16, true, 128>; },
+           std::bool_constant<RAW>(), lds, 1024);
     } else {
       const size_t lds = gram_dma_lds<Tin, MT, NT, 128>(rows, w);
-      go_w(gram_dma_kernel<Tin, MT, MODE, 3, WW, NB, NT, 16, false, 128>,
-           gram_dma_kernel<Tin, MT, MODE, 3, false, NB, NT, 16, false, 128>, lds, 1024);
+      go_w([](auto wc) { return gram_dma_kernel<Tin, MT, MODE, 3, decltype(wc)::value, NB, NT, 16, false, 128>; },
+           std::bool_constant<RAW>(), lds, 1024);
     }
     return true;
   }
