@@ -194,11 +194,15 @@ def make_iso(iso: dict | None):
 
 
 def _stream_ptr(stream):
-    if stream is not None:
-        return ctypes.c_void_p(stream.cuda_stream)
-    # the current stream of the current device, without the Stream object
-    # torch.cuda.current_stream() builds (2.7 us of a small call's 40)
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    if stream is None:
+        # the current stream of the current device, without the Stream object
+        # torch.cuda.current_stream() builds (2.7 us of a small call's 40); a
+        # private function of torch, hence the other way where it is missing
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return ctypes.c_void_p(raw(torch.cuda.current_device()))
+        stream = torch.cuda.current_stream()
+    return ctypes.c_void_p(stream.cuda_stream)
 
 
 def pid_workspace_size(U, weights=None, iso=None, variant=0, gemm="auto") -> int:
