@@ -36,8 +36,9 @@ METRIC = "all-pairs PID pair·points/s (MFMA vs FP32) at ≤1e-4 err; PID-mean G
 HBM_PEAK_GBPS = 8000.0
 TIME_EVERY = 4   # the Gram kernel is bracketed by events on every 4th timed launch
 ROTATE = 4       # resident copies of the headline batch the timed steps cycle over
-KERNEL_SOURCES = ["paper_2512_15187_amd/csrc/gram_kernel.h", "paper_2512_15187_amd/csrc/device_common.h",
-                  "paper_2512_15187_amd/csrc/k_gram.hip", "paper_2512_15187_amd/csrc/k_gram_f32.hip"]
+_CSRC = "paper_2512_15187_amd/csrc/"
+KERNEL_SOURCES = [_CSRC + "gram_kernel.h", _CSRC + "gram_cover.h", _CSRC + "device_common.h", _CSRC + "pid_internal.h",
+                  _CSRC + "pid_timing.h", "include/pid.h", _CSRC + "k_gram.hip", _CSRC + "k_gram_f32.hip"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "gram_f16_2d_n256_m262144_traffic.txt")
 
 
