@@ -85,7 +85,7 @@ typedef enum {
 /* Arithmetic of the all-pairs numerators G_ij = sum_x w u_i u_j. */
 typedef enum {
   PID_GEMM_AUTO = 0,        /* I8 for unweighted binary input, F64 for F64 input, else F16    */
-  PID_GEMM_F64 = 1,         /* FP64 vector FMA                                                */
+  PID_GEMM_F64 = 1,         /* FP64 matrix cores (161 to 256 members: FP64 vector FMA)        */
   PID_GEMM_F32 = 2,         /* FP32 vector FMA (plain FP32 comparator)                        */
   PID_GEMM_F16 = 3,         /* FP16 MFMA, FP32 accumulation (inputs rounded to FP16 once)     */
   PID_GEMM_BF16 = 4,        /* BF16 MFMA, FP32 accumulation (inputs rounded to BF16 once)     */
@@ -102,8 +102,9 @@ typedef enum {
                                  value, say) gives unspecified depths, not an error     */
 
 /* The ensemble: N members x M grid points, member-major.  Element (i, x) is at
- * data[i * ld + x] (ld >= M, in elements).  Rows whose byte address is a
- * multiple of 16 take the vectorised path; others are read element by element.
+ * data[i * ld + x] (ld >= M, in elements), at any alignment of the element.
+ * All rows are read 16 bytes at a time; those whose byte address is a multiple
+ * of 16 can also be staged straight into LDS, which is faster in places.
  * weights: M floats (w_x >= 0), or NULL for a uniform grid (w = 1). */
 typedef struct {
   int64_t n;
@@ -174,8 +175,10 @@ pid_status pid_all_pairs(const pid_ensemble* ens, const pid_iso* iso, int gemm,
  * B (IN_in stays exact).  out->inclusion is ignored; the other fields as
  * pid_all_pairs.  Workspace: pid_workspace_size(variant 3).  For large N, where
  * the Gram product's N^2 M work dominates, this reads the masks three times
- * instead (four beyond 256 members, where the PID-mean pass itself takes a
- * column-sum read and a row-sum read). */
+ * instead.  Beyond 256 members (FP64: 128) the PID-mean pass itself takes a
+ * column-sum read and a row-sum read: soft masks still take three reads there
+ * (masses beside the column sums, and one row pass against s and t together),
+ * fields and binary input four. */
 pid_status pid_pairs_depths(const pid_ensemble* ens, const pid_iso* iso, const pid_out* out,
                             void* workspace, size_t ws_bytes, void* stream);
 

@@ -296,7 +296,7 @@ __global__ __launch_bounds__(512) void gram_kernel(GramArgs a) {
     }
   }
 
-  // FP64 of up to two sub-tiles per wave (one super-tile of up to 4 row blocks,
+  // FP64 of up to two sub-tiles per wave (one super-tile of up to 5 row blocks,
   // or several): the sub-tiles as quarters of 16x16 on the FP64 matrix cores,
   // dealt out one by one, so that few sub-tiles still give every wave work
   // (n = 50: 12 quarters for 8 waves).  With five sub-tiles per wave the

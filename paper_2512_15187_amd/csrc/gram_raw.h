@@ -438,7 +438,7 @@ __global__ __launch_bounds__(512, 2) void gram_raw_tri_kernel(GramArgs a) {
 // 165).  MC x 128 rows are summed; LW load instructions per wave and slab (a
 // unit of fewer rows uses fewer).  Whole calls, gram_raw_kernel and this one:
 // n = 288 on 640^2 166 -> 98 us, n = 400 on 704x640 322 -> 159, n = 384 on
-// 960^2 489 -> 268, n = 512 on 1024^2 460 -> 405..428 (1.07 GB); beside the
+// 960^2 489 -> 268, n = 512 on 1024^2 460 -> 397 (1.07 GB); beside the
 // converting kernel n = 256 on 1024^2 148 -> 132.
 template <typename Tin, int MT, int LW, int NT, int MC>
 __global__ __launch_bounds__(1024) void gram_raw_cover_kernel(GramArgs a, RawCover cv) {
@@ -511,7 +511,7 @@ __global__ __launch_bounds__(1024) void gram_raw_cover_kernel(GramArgs a, RawCov
   // Even waves fetch three slabs ahead, odd ones two: what is in flight comes
   // from two places of each row, which a row stride of a large power of two
   // would otherwise put on few memory channels (n = 512 on 1024^2: 458 us
-  // all three ahead, 405 so; all else the same within 3 %).
+  // all three ahead, 397 so; all else the same within 3 %).
   const int la = NB - 1 - (wave & 1);
   const int left = (la - 1) * lw;      // loads of this wave that may stay in flight past slab j's
   for (int j = 0; j < la; ++j) issue(j, j);

@@ -327,7 +327,7 @@ size_t pairs_linear_workspace(int64_t n, int64_t m, int dtype, int iso_kind, boo
 
 // Bit-packed binary PID-mean (k_bits.hip): groups of 255 members for the
 // column counts, KT planes for counts up to n, row tiles of 64 lanes x WPL
-// words (WPL = 4 up to 16 planes, 2 beyond), 64 members per block.
+// words (WPL = 4 up to 16 planes, 2 beyond), 8 to 32 members per wave.
 B1Plan b1_plan(int64_t n, int64_t m) {
   B1Plan p{};
   p.W = (m + 31) / 32;
